@@ -8,8 +8,8 @@
 
 namespace spork {
 
-// bf16: head_dim 128, 16- or 32-token blocks, workgroups of 4 or 8 waves with
-// one or two row tiles per wave; fp32: head_dim 64 or 128, 16- or 32-token
+// bf16: head_dim 128, 16- or 32-token blocks, workgroups of 4 (narrow) or 8
+// (wide) waves with up to two 16-row tiles per wave; fp32: head_dim 64 or 128, 16- or 32-token
 // blocks, one wave with up to 4 row tiles. The kernel table in
 // attention.hip instantiates exactly these.
 bool attention_supported(int32_t dtype, int32_t head_dim, int32_t block_size, int32_t row_tiles, int32_t waves) {
