@@ -77,6 +77,20 @@ __device__ __forceinline__ float load_f(const uint16_t* p, int i) {
   return __uint_as_float(static_cast<uint32_t>(p[i]) << 16);
 }
 
+// 16 bytes that the launch reads once: a non-temporal load.
+__device__ __forceinline__ uint4 load_stream(const uint4* p) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
+}
+
+// Element j of the 16-byte vector u.
+template <typename T>
+__device__ __forceinline__ float vec_f(const uint4& u, int j) {
+  const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+  if constexpr (sizeof(T) == 4) return __uint_as_float(w[j]);
+  else return __uint_as_float(j & 1 ? w[j >> 1] & 0xFFFF0000u : w[j >> 1] << 16);
+}
+
 // Online (max, sum of 2^((x - max) log2 e)) of a set of logits; an empty set
 // or one holding only -inf is (-inf, 0).
 struct MaxSum {
@@ -110,37 +124,90 @@ __device__ __forceinline__ void argmax_unit(const T* x, int vocab, int chunks, i
     const int lo = static_cast<int>(static_cast<int64_t>(nv) * c / chunks);
     const int hi = static_cast<int>(static_cast<int64_t>(nv) * (c + 1) / chunks);
     const uint4* xv = reinterpret_cast<const uint4*>(x);
-    auto scan = [&](const uint4& u, int v) __attribute__((always_inline)) {
-      const T* e = reinterpret_cast<const T*>(&u);
+    // Groups of 16-byte loads in flight together, taken in index order: 1024
+    // per workgroup (at least four per thread), then the remainder. The
+    // scan compares once per vector and keeps the vector of the first strict
+    // maximum, in registers (loading it again at the end costs a trip to HBM);
+    // its element is looked up once, below. The running sum is rescaled once
+    // per group.
+    int bvec = -1;
+    uint4 bu = make_uint4(0, 0, 0, 0);
+    auto scan = [&](const auto& u, int v) __attribute__((always_inline)) {
+      constexpr int G = sizeof(u) / sizeof(uint4);
+      float gm = kNegInf;
 #pragma unroll
-      for (int j = 0; j < VEC; ++j) {
-        const float val = load_f(e, j);
-        if (val > best || bidx == INT_MAX) {
-          best = val;
-          bidx = v * VEC + j;
+      for (int g = 0; g < G; ++g) {
+        float vm = vec_f<T>(u[g], 0);
+        if (bvec < 0) {  // a NaN in the very first element stays the maximum
+          bvec = v;
+          best = vm;
+          bu = u[g];
         }
+#pragma unroll
+        for (int j = 1; j < VEC; ++j) vm = fmaxf(vm, vec_f<T>(u[g], j));
+        if (vm > best) {
+          best = vm;
+          bvec = v + g * NT;
+          bu = u[g];
+        }
+        if constexpr (kSum) gm = fmaxf(gm, vm);
       }
       if constexpr (kSum) {
-        float vm = load_f(e, 0);
+        const float nm = fmaxf(acc.m, gm);
+        auto terms = [&](auto power) __attribute__((always_inline)) {
+          float t = 0.0f;
 #pragma unroll
-        for (int j = 1; j < VEC; ++j) vm = fmaxf(vm, load_f(e, j));
-        const float nm = fmaxf(acc.m, vm);
-        float t = 0.0f;
+          for (int g = 0; g < G; ++g) {
+            float tv = 0.0f;
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) t += exp2_fast((load_f(e, j) - nm) * kLog2e);
+            for (int j = 0; j < VEC; ++j) tv += exp2_fast(power(vec_f<T>(u[g], j)));
+            t += tv;
+          }
+          return t;
+        };
+        // Ordinary logits: (x - nm) log2 e as one fused multiply-add. The
+        // rounding error of nm log2 e is common to the group's terms and is
+        // taken out of their sum (below 1e-4 here, so to first order). Larger
+        // maxima, masks of the type's lowest value, infinities and NaN:
+        // subtracted first.
+        float t;
+        if (fabsf(nm) < 1024.0f) {
+          const float c0 = nm * kLog2e, err = fmaf(nm, kLog2e, -c0);
+          t = terms([&](float x) { return fmaf(x, kLog2e, -c0); });
+          t = fmaf(t, -err * kLn2, t);
+        } else {
+          t = terms([&](float x) { return (x - nm) * kLog2e; });
+        }
         acc.add_max(nm, t);
       }
     };
-    // four 16-byte loads in flight per thread, scanned in index order
     int v = lo + static_cast<int>(threadIdx.x);
-    for (; v + 3 * NT < hi; v += 4 * NT) {
-      const uint4 u0 = xv[v], u1 = xv[v + NT], u2 = xv[v + 2 * NT], u3 = xv[v + 3 * NT];
-      scan(u0, v);
-      scan(u1, v + NT);
-      scan(u2, v + 2 * NT);
-      scan(u3, v + 3 * NT);
+    auto sweep = [&](auto group) __attribute__((always_inline)) {
+      constexpr int G = decltype(group)::value, kScan = G < 4 ? G : 4;
+      for (; v + (G - 1) * NT < hi; v += G * NT) {
+        uint4 u[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) u[g] = load_stream(xv + v + g * NT);
+        // at most four vectors a scan: their elements, unpacked, stay in registers
+#pragma unroll
+        for (int g = 0; g < G; g += kScan) {
+          uint4 part[kScan];
+#pragma unroll
+          for (int i = 0; i < kScan; ++i) part[i] = u[g + i];
+          scan(part, v + g * NT);
+        }
+      }
+    };
+    constexpr int kGroup = NT >= 128 ? 4 : 1024 / NT;
+    sweep(std::integral_constant<int, kGroup>{});
+    if constexpr (kGroup > 4) sweep(std::integral_constant<int, kGroup / 4>{});
+    sweep(std::integral_constant<int, 1>{});
+    if (bvec >= 0) {  // the lowest element of the vector that is the maximum
+      int at = 0;  // a NaN is the first
+#pragma unroll
+      for (int j = VEC - 1; j >= 0; --j) at = vec_f<T>(bu, j) == best ? j : at;
+      bidx = bvec * VEC + at;
     }
-    for (; v < hi; v += NT) scan(xv[v], v);
   } else {
     const int lo = static_cast<int>(static_cast<int64_t>(vocab) * c / chunks);
     const int hi = static_cast<int>(static_cast<int64_t>(vocab) * (c + 1) / chunks);

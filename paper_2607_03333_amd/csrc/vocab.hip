@@ -31,11 +31,16 @@ __global__ void __launch_bounds__(64) accept_kernel(AcceptArgs a) { accept_unit(
 // the span's rows after its first, its exponential (1 for an empty set) and
 // the gate. Span offsets are clamped to [0, n_rows]; a reversed span is empty.
 // --------------------------------------------------------------------------
+// Threads of a confidence workgroup. The pass has 2048 to 4095 (row, chunk)
+// units where rows are few; at 128 threads the chip holds 4096 of them at
+// once, at 256 threads 2048 and the few left over ran alone at the end.
+constexpr int kConfThreads = 128;
+
 template <typename T>
-__global__ void __launch_bounds__(256) conf_chunks(ConfArgs a) {
+__global__ void __launch_bounds__(kConfThreads) conf_chunks(ConfArgs a) {
   const int row = blockIdx.x / a.chunks, c = blockIdx.x % a.chunks;
   const size_t u = static_cast<size_t>(row) * a.chunks + c;
-  argmax_unit<T, 256, true>(static_cast<const T*>(a.logits) + static_cast<size_t>(row) * a.vocab, a.vocab, a.chunks,
+  argmax_unit<T, kConfThreads, true>(static_cast<const T*>(a.logits) + static_cast<size_t>(row) * a.vocab, a.vocab, a.chunks,
                             c, a.keys + u, reinterpret_cast<float2*>(a.ms) + u);
 }
 
@@ -98,9 +103,9 @@ hipError_t launch_argmax(const AcceptArgs& a, hipStream_t stream) {
 hipError_t launch_conf_chunks(const ConfArgs& a, hipStream_t stream) {
   if (a.n_rows == 0) return hipSuccess;
   if (a.logits_dtype == 1)
-    hipLaunchKernelGGL(conf_chunks<uint16_t>, dim3(a.n_rows * a.chunks), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(conf_chunks<uint16_t>, dim3(a.n_rows * a.chunks), dim3(kConfThreads), 0, stream, a);
   else
-    hipLaunchKernelGGL(conf_chunks<float>, dim3(a.n_rows * a.chunks), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(conf_chunks<float>, dim3(a.n_rows * a.chunks), dim3(kConfThreads), 0, stream, a);
   return hipGetLastError();
 }
 
