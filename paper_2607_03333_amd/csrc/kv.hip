@@ -1,13 +1,19 @@
-// gfx950 setup kernels: token scatter into the paged KV pools and the block
-// copy of copy-on-write (Section 4.1). Not on the timed path.
+// gfx950 kernels around a step: token scatter into the paged KV pools, the
+// block copy of copy-on-write (Section 4.1) and the patch of a plan's image.
 #include "device_common.h"
 
 namespace spork {
 namespace {
 
-// --------------------------------------------------------------------------
-// Setup kernels.
-// --------------------------------------------------------------------------
+// Fewest (token, KV head) pairs of a call that goes a block at a time. Below,
+// the scatter by token has more threads to hide the stores' latency with (bf16,
+// 128 channels, 512 tokens of 512 sequences, 8 heads: 7.4 us against 8.0; 272
+// tokens in runs of 17: 5.3 against 4.9; 816 tokens, 4 heads: both 5.4). Above,
+// the 2-byte stores bound it (8 heads: 576 tokens in runs of 9: 8.0 us against
+// 6.2; 1600 single tokens: 27.9 against 15.5; 4000 in a row: 35.4 against 9.3).
+constexpr int64_t kBlocksMin = 4608;
+
+// Scatter by token: a thread per 16-byte chunk of a token and head.
 template <typename T>
 __global__ void __launch_bounds__(256) kv_write_kernel(int hkv, int D, int BS, int64_t num_slots, T* kc,
                                                        T* vc, const int64_t* slots, const T* kn,
@@ -34,6 +40,106 @@ __global__ void __launch_bounds__(256) kv_write_kernel(int hkv, int D, int BS, i
   for (int e = 0; e < VEC; ++e) vd[static_cast<size_t>(cchunk * VEC + e) * BS] = vs[e];
 }
 
+// --------------------------------------------------------------------------
+// The scatter of many tokens, a block at a time: one wave per (window of BS
+// tokens, KV head). The V pool holds a block transposed ([D][BS]), so a token's
+// channels lie BS elements apart and the kernel above stores them one by one;
+// here the wave transposes its window through LDS, and a window whose tokens
+// fill one block in order (all but the ends of an appended run) goes out as
+// contiguous 16-byte stores. The windows are laid out from the offset of the
+// first token in its block. Any other window stores V by element, tokens
+// fastest.
+// LDS: dword rows of D channels; a bf16 row holds a pair of tokens (packed in
+// registers), an fp32 row one. A 16-byte piece of the pool is the same channel
+// of four rows; the padding puts the pieces that a wave reads at once into
+// different banks (fp32 with 32-token blocks: two lanes per bank).
+// Bound by the stream from and to HBM: 15,001 tokens of 8 heads of 128 bf16
+// channels 149 us by element stores, 38.8 us by blocks, 23.6 us (5.2 TB/s)
+// with non-temporal loads, which leave the caches to the stores. Non-temporal
+// stores too: 21.9 us, but the attention that follows reads the blocks.
+// --------------------------------------------------------------------------
+template <typename T, int D, int BS>
+__global__ void __launch_bounds__(64) kv_write_blocks(int hkv, int64_t num_slots, T* kc, T* vc, const int64_t* slots,
+                                                      const T* kn, const T* vn, int n, int* bad) {
+  constexpr int VEC = 16 / sizeof(T), CH = D / VEC;  // 16-byte chunks of a token
+  constexpr int PACK = 4 / sizeof(T);                // tokens of an LDS row
+  constexpr int R = BS / PACK, QN = R / 4;           // rows; pieces per channel
+  constexpr int STRIDE = D + (QN == 2 ? 8 : 4);
+  constexpr int KIT = BS * CH / 64, VIT = R * CH / 64, OIT = D * QN / 64;
+  __shared__ uint32_t tile[R * STRIDE];
+  const int lane = threadIdx.x;
+  const int h = static_cast<int>(blockIdx.x % static_cast<unsigned>(hkv));
+  const int64_t s0 = slots[0];
+  const int shift = s0 < 0 ? 0 : static_cast<int>(s0 % BS);
+  const int64_t i0 = static_cast<int64_t>(blockIdx.x / static_cast<unsigned>(hkv)) * BS - shift;
+  if (i0 >= n) return;
+  const auto has = [&](int t) { return i0 + t >= 0 && i0 + t < n; };
+  const auto src = [&](const T* x, int t, int c) {
+    return reinterpret_cast<const uint4*>(x + (static_cast<size_t>(i0 + t) * hkv + h) * D + c * VEC);
+  };
+  const uint4 zero = make_uint4(0, 0, 0, 0);
+  uint4 vr[VIT][PACK], kr[KIT];
+#pragma unroll
+  for (int it = 0; it < VIT; ++it) {
+    const int r = (it * 64 + lane) / CH, c = lane % CH;
+#pragma unroll
+    for (int p = 0; p < PACK; ++p) vr[it][p] = has(r * PACK + p) ? load_stream(src(vn, r * PACK + p, c)) : zero;
+  }
+#pragma unroll
+  for (int it = 0; it < KIT; ++it) {
+    const int t = (it * 64 + lane) / CH;
+    kr[it] = has(t) ? load_stream(src(kn, t, lane % CH)) : zero;
+  }
+  // lane t (and t + BS, ...): the slot of token t
+  const int tt = lane % BS;
+  const int64_t slot = has(tt) ? slots[i0 + tt] : -1;
+  const bool ok = slot >= 0 && slot < num_slots;
+  if (bad != nullptr && h == 0 && lane < BS && has(tt) && !ok) atomicAdd(bad, 1);
+#pragma unroll
+  for (int it = 0; it < VIT; ++it) {
+    const int r = (it * 64 + lane) / CH, c = lane % CH;
+    uint32_t* row = tile + r * STRIDE + c * VEC;
+    if constexpr (PACK == 1) {
+      *reinterpret_cast<uint4*>(row) = vr[it][0];
+    } else {
+      const uint4 a = vr[it][0], b = vr[it][1];
+      const auto lo2 = [](uint32_t x, uint32_t y) { return (x & 0xFFFFu) | (y << 16); };
+      const auto hi2 = [](uint32_t x, uint32_t y) { return (x >> 16) | (y & 0xFFFF0000u); };
+      *reinterpret_cast<uint4*>(row) = make_uint4(lo2(a.x, b.x), hi2(a.x, b.x), lo2(a.y, b.y), hi2(a.y, b.y));
+      *reinterpret_cast<uint4*>(row + 4) = make_uint4(lo2(a.z, b.z), hi2(a.z, b.z), lo2(a.w, b.w), hi2(a.w, b.w));
+    }
+  }
+  __syncthreads();
+  const int64_t first = __shfl(slot, 0);
+  const bool whole = __all(ok && slot == first + tt) && first % BS == 0;
+  if (whole) {
+    const size_t base = (static_cast<size_t>(first / BS) * hkv + h) * (D * BS);
+    uint4* kd = reinterpret_cast<uint4*>(kc + base);
+    uint4* vd = reinterpret_cast<uint4*>(vc + base);
+#pragma unroll
+    for (int it = 0; it < KIT; ++it) kd[it * 64 + lane] = kr[it];
+#pragma unroll
+    for (int it = 0; it < OIT; ++it) {
+      const int d = (it * 64 + lane) / QN, q = lane % QN;
+      const uint32_t* col = tile + 4 * q * STRIDE + d;
+      vd[it * 64 + lane] = make_uint4(col[0], col[STRIDE], col[2 * STRIDE], col[3 * STRIDE]);
+    }
+    return;
+  }
+#pragma unroll
+  for (int it = 0; it < KIT; ++it) {
+    const int64_t ks = __shfl(slot, (it * 64 + lane) / CH);
+    if (ks >= 0 && ks < num_slots)
+      *reinterpret_cast<uint4*>(kc + ((static_cast<size_t>(ks / BS) * hkv + h) * BS + ks % BS) * D + lane % CH * VEC) =
+          kr[it];
+  }
+  if (!ok) return;
+  T* vd = vc + (static_cast<size_t>(slot / BS) * hkv + h) * (D * BS) + slot % BS;
+  const T* col = reinterpret_cast<const T*>(tile + tt / PACK * STRIDE) + tt % PACK;
+#pragma unroll 8
+  for (int d = lane / BS; d < D; d += 64 / BS) vd[static_cast<size_t>(d) * BS] = col[d * PACK];
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256) kv_copy_kernel(int hkv, int D, int BS, T* kc, T* vc, int src, int dst,
                                                       int nv) {
@@ -56,6 +162,16 @@ __global__ void __launch_bounds__(256) image_patch_kernel(int32_t* image, ImageP
   for (int i = threadIdx.x; i < patch.n; i += 256) image[patch.off[i]] = patch.val[i];
 }
 
+template <typename T>
+void write_blocks(int hkv, int d, int bs, int64_t num_slots, T* kc, T* vc, const int64_t* slots, const T* kn,
+                  const T* vn, int n, int* bad, hipStream_t stream) {
+  // one window more than n / bs rounded up: the first may hold a single token
+  const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(n) + 2 * bs - 2) / bs * hkv));
+  auto* k = d == 128 ? (bs == 16 ? kv_write_blocks<T, 128, 16> : kv_write_blocks<T, 128, 32>)
+                     : (bs == 16 ? kv_write_blocks<T, 64, 16> : kv_write_blocks<T, 64, 32>);
+  hipLaunchKernelGGL(k, grid, dim3(64), 0, stream, hkv, num_slots, kc, vc, slots, kn, vn, n, bad);
+}
+
 }  // namespace
 
 hipError_t launch_image_patch(int32_t* image, const ImagePatch& patch, hipStream_t stream) {
@@ -69,6 +185,16 @@ hipError_t launch_kv_write(int32_t dtype, int32_t hkv, int32_t head_dim, int32_t
                            const void* k_new, const void* v_new, int32_t n, int32_t* bad_slots,
                            hipStream_t stream) {
   if (n == 0) return hipSuccess;
+  if (static_cast<int64_t>(n) * hkv >= kBlocksMin && (head_dim == 64 || head_dim == 128) && (block_size == 16 || block_size == 32)) {
+    if (dtype == 1)
+      write_blocks(hkv, head_dim, block_size, num_slots, static_cast<uint16_t*>(k_cache),
+                   static_cast<uint16_t*>(v_cache), slots, static_cast<const uint16_t*>(k_new),
+                   static_cast<const uint16_t*>(v_new), n, bad_slots, stream);
+    else
+      write_blocks(hkv, head_dim, block_size, num_slots, static_cast<float*>(k_cache), static_cast<float*>(v_cache),
+                   slots, static_cast<const float*>(k_new), static_cast<const float*>(v_new), n, bad_slots, stream);
+    return hipGetLastError();
+  }
   const int vec = dtype == 1 ? 8 : 4;
   const int64_t total = static_cast<int64_t>(n) * hkv * (head_dim / vec);
   const dim3 grid(static_cast<unsigned>((total + 255) / 256));

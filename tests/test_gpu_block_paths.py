@@ -3,12 +3,55 @@ scatter by whole blocks, the confidence pass over masked logits and the n-gram
 scan of one chunk per sequence."""
 import numpy as np
 import pytest
+import torch
 
-from paper_2607_03333_amd import synth
+from oracle.kv import scatter_tokens
+from paper_2607_03333_amd import spork, synth
 from gpu_cases import say
 from test_gpu_confidence import THETA, check as check_confidence
+from test_gpu_kv import _dev, _host, _pools
 
 pytestmark = pytest.mark.gpu
+
+
+def _runs(rng, nb, bs, lens):
+    """Slots of appended runs, each from a random offset of its first block; no slot twice."""
+    blocks, out = rng.permutation(nb).tolist(), []
+    for n in lens:
+        off = int(rng.integers(0, bs))
+        own = [blocks.pop() for _ in range((off + n + bs - 1) // bs)]
+        out += [own[(off + i) // bs] * bs + (off + i) % bs for i in range(n)]
+    return np.array(out, dtype=np.int64)
+
+
+@pytest.mark.parametrize("dtype,hkv,d,bs", [(synth.F32, 2, 64, 16), (synth.F32, 1, 128, 32), (synth.BF16, 4, 128, 16),
+                                            (synth.BF16, 8, 128, 32), (synth.BF16, 3, 64, 16), (synth.F32, 2, 128, 16),
+                                            (synth.F32, 2, 64, 32), (synth.BF16, 2, 64, 32)])
+@pytest.mark.parametrize("kind", ["below", "least", "one run", "runs", "bad slots", "single tokens"])
+def test_kv_write_of_many_tokens_is_exact(dtype, hkv, d, bs, kind):
+    least = -(-4608 // hkv)  # tokens of the smallest call that goes by blocks
+    lens = {"below": [least - 1], "least": [least], "one run": [least + 277],
+            "runs": [least - 400, 1, 15, 16, 17, 31, 32, 33, 333, 2], "bad slots": [least + 50],
+            "single tokens": [1] * (least + 6)}[kind]
+    bad = (0, 77, least + 49) if kind == "bad slots" else ()
+    rng = np.random.default_rng(len(lens) * 100 + d + bs + hkv)
+    nb = sum(n // bs + 2 for n in lens) + 3
+    k, v = _pools(rng, dtype, nb, hkv, bs, d)
+    dk, dv = _dev(k), _dev(v)
+    slots = _runs(rng, nb, bs, lens)
+    for i, j in enumerate(bad):
+        slots[j] = (-1, nb * bs, -(1 << 40))[i]
+    kt, vt = (np.ascontiguousarray(x.reshape(len(slots), hkv, d)) for x in _pools(rng, dtype, len(slots), hkv, 1, d))
+    shape = spork.make_shape(hkv, hkv, d, bs, spork.SPORK_DTYPE_F32 if dtype == synth.F32 else spork.SPORK_DTYPE_BF16,
+                             1.0)
+    counter = torch.zeros(1, dtype=torch.int32, device="cuda")
+    say(f"  kv write {dtype} hkv={hkv} d={d} bs={bs} n={len(slots)} runs={len(lens)} bad={len(bad)}")
+    spork.spork_kv_write(shape, dk, dv, nb, torch.from_numpy(slots).cuda(), _dev(kt), _dev(vt), counter)
+    torch.cuda.synchronize()
+    valid = (slots >= 0) & (slots < nb * bs)
+    scatter_tokens(k, v, slots[valid], kt[valid], vt[valid])
+    assert int(counter.item()) == len(bad)
+    assert np.array_equal(_host(dk, k), k) and np.array_equal(_host(dv, v), v)
 
 
 @pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
