@@ -728,7 +728,8 @@ int spork_ngram_propose(const int32_t* tokens, const int64_t* seq_off, int32_t n
     const int rc = hip_status(
         timed(SPORK_KERNEL_NGRAM_SCAN, stream, [&] { return spork::launch_ngram_scan(a, stream); }),
         "spork_ngram_propose (scan)");
-    if (rc != SPORK_OK) return rc;
+    // one chunk per sequence: the scan has written the drafts
+    if (rc != SPORK_OK || a.n_chunks == 1) return rc;
     return hip_status(timed(SPORK_KERNEL_NGRAM_DRAFTS, stream, [&] { return spork::launch_ngram_drafts(a, stream); }),
                       "spork_ngram_propose (drafts)");
   });

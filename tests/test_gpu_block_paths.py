@@ -5,11 +5,13 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from oracle.kv import scatter_tokens
 from paper_2607_03333_amd import spork, synth
 from gpu_cases import say
 from test_gpu_confidence import THETA, check as check_confidence
 from test_gpu_kv import _dev, _host, _pools
+from test_gpu_ngram import check as check_ngram
 
 pytestmark = pytest.mark.gpu
 
@@ -76,3 +78,15 @@ def test_confidence_of_masked_and_large_logits(dtype, vocab, mask):
         x = (np.ascontiguousarray(x).view(np.uint32) >> 16).astype(np.uint16)
     say(f"confidence {mask} {dtype} V={vocab}")
     check_confidence(x, dtype, b.span_off, THETA, tag=f"{mask} {dtype} V={vocab}")
+
+
+@pytest.mark.parametrize("n_min,n_max,k", [(1, 1, 1), (1, 32, 50), (3, 8, 300)])
+def test_ngram_one_chunk_per_sequence(n_min, n_max, k):
+    rng = np.random.default_rng(n_max)
+    lens = [0, 1, 2, 31, 32, 33, 34, 255, 256, 257, 1999, 2047, 2048]
+    seqs = [rng.integers(0, 2 + i % 3, size=n).astype(np.int32) for i, n in enumerate(lens)]
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    check_ngram(np.concatenate(seqs), off, n_min, n_max, k, tag=f"one chunk n {n_min}-{n_max} k {k}")
+    # longer than the declared maximum: still scanned whole
+    check_ngram(np.tile(seqs[-1], 3), np.array([0, 6144]), n_min, n_max, k, max_len=100, tag="past max_len")
+    assert oracle.ngram_propose([seqs[-1]], n_min, n_max, k)[1][0] > 0
