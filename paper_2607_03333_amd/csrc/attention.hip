@@ -351,6 +351,19 @@ struct StageLoader {
   }
 };
 
+// Argmax unit u (row x vocabulary chunk) of a verify step.
+template <int NT>
+__device__ __forceinline__ void verify_argmax_unit(const AcceptArgs& acc, int u) {
+  const int row = u / acc.chunks, c = u % acc.chunks;
+  uint64_t* key = acc.keys + static_cast<size_t>(row) * acc.chunks + c;
+  const size_t roff = static_cast<size_t>(row) * acc.vocab;
+  if (acc.logits_dtype == 1)
+    argmax_unit<uint16_t, NT, false>(static_cast<const uint16_t*>(acc.logits) + roff, acc.vocab, acc.chunks, c, key,
+                                     nullptr);
+  else
+    argmax_unit<float, NT, false>(static_cast<const float*>(acc.logits) + roff, acc.vocab, acc.chunks, c, key, nullptr);
+}
+
 // Verify step: the greedy argmax over the logits fills the tail of the
 // launch. Workgroups whose lists are done take (row, chunk) units from one
 // shared cursor, so the compute units that finish early stream the logits
@@ -364,15 +377,7 @@ __device__ __forceinline__ void argmax_tail(const AttnArgs& a, int tid, int& nex
     __syncthreads();
     const int u = __builtin_amdgcn_readfirstlane(next_unit);
     if (u < 0 || u >= a.tail_units) break;
-    const int row = u / a.acc.chunks, c = u % a.acc.chunks;
-    uint64_t* key = a.acc.keys + static_cast<size_t>(row) * a.acc.chunks + c;
-    const size_t roff = static_cast<size_t>(row) * a.acc.vocab;
-    if (a.acc.logits_dtype == 1)
-      argmax_unit<uint16_t, NT, false>(static_cast<const uint16_t*>(a.acc.logits) + roff, a.acc.vocab, a.acc.chunks, c,
-                                        key, nullptr);
-    else
-      argmax_unit<float, NT, false>(static_cast<const float*>(a.acc.logits) + roff, a.acc.vocab, a.acc.chunks, c, key,
-                                     nullptr);
+    verify_argmax_unit<NT>(a.acc, u);
     // The unit ends with thread 0 storing the key and the next take starts
     // with thread 0 taking a unit: this barrier keeps the two thread-0
     // regions apart, so the compiler cannot join them across the loop's
@@ -1097,6 +1102,10 @@ __global__ void __launch_bounds__(64) attn_f32(AttnArgs a) {
   static_assert(D % 16 == 0 && (BS == 16 || BS == 32 || BS == 64), "unsupported shape");
   constexpr int KS = D / 4;
   constexpr int DT = D / 16;
+  if (static_cast<int>(blockIdx.x) >= a.grid) {  // a verify step's argmax, beside the attention
+    verify_argmax_unit<64>(a.acc, blockIdx.x - a.grid);
+    return;
+  }
   const WaveDesc w = a.waves[blockIdx.x];
   if (w.item < 0) return;
   const ItemDesc it = a.items[w.item];
@@ -1398,7 +1407,8 @@ hipError_t launch_attn_partial(const AttnArgs& a, hipStream_t stream) {
   AttnKernel k = pick_attention(a.dtype, a.head_dim, a.block_size, a.row_tiles, a.wg_waves);
   if (k == nullptr) return hipErrorInvalidValue;
   const int threads = a.dtype == 1 ? 64 * a.wg_waves : 64;
-  if (a.grid > 0) hipLaunchKernelGGL(k, dim3(a.grid), dim3(threads), 0, stream, a);
+  const int grid = a.dtype == 1 ? a.grid : a.grid + a.tail_units;
+  if (grid > 0) hipLaunchKernelGGL(k, dim3(grid), dim3(threads), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -450,9 +450,8 @@ int spork_workspace_clear(const spork_plan* plan, void* workspace, size_t ws_byt
   });
 }
 
-// Attention over a plan. bf16 (persistent): the attention launch (with the
-// argmax units of a verify step in its tail), then the merge launch (with
-// the accept). fp32: the argmax first (verify), the attention, the merge.
+// Attention over a plan: the attention launch (with the argmax units of a
+// verify step in its tail), then the merge launch (with the accept).
 // Checks of the attention arguments that come before anything is launched.
 static int check_attention(const spork_plan* plan, const void* dev_image, const void* q, const void* k_cache,
                            const void* v_cache, const void* out) {
@@ -510,22 +509,17 @@ static int attention(const spork_plan* plan, const void* dev_image, const void* 
   a.part_ml = reinterpret_cast<float*>(ws + p.off_ws_ml);
   a.n_cursors = p.n_cursors;
   // The persistent bf16 kernel takes its units through cursors that are zero
-  // on entry (the merge launch clears them again); in a verify step it also
-  // runs the argmax units after its lists, and the accept rides in the merge
-  // launch: two launches. The fp32 kernel is not persistent: the argmax has
-  // a launch of its own first.
-  const bool persistent = p.shape.persistent;
+  // on entry (the merge launch clears them again). In a verify step it also
+  // runs the argmax units after its lists; the fp32 kernel, one workgroup per
+  // unit, runs them as workgroups of their own behind the attention's. The
+  // accept rides in the merge launch: two launches. (fp32, 1 session, 5 rows
+  // of 512 logits: an argmax launch of its own took 3 us of the step's 22.)
   const bool verify = acc != nullptr && acc->n_verify > 0;
-  int rc = SPORK_OK;
-  if (verify) a.acc = *acc;
-  if (persistent) {
-    if (verify) a.tail_units = acc->n_verify * (acc->k_drafts + 1) * acc->chunks;
-  } else if (verify) {
-    rc = hip_status(timed(SPORK_KERNEL_ARGMAX, stream, [&] { return spork::launch_argmax(a.acc, stream); }),
-                    "spork_verify_accept (argmax)");
+  if (verify) {
+    a.acc = *acc;
+    a.tail_units = acc->n_verify * (acc->k_drafts + 1) * acc->chunks;
   }
-  if (rc != SPORK_OK) return rc;
-  rc = hip_status(timed(SPORK_KERNEL_ATTN, stream, [&] { return spork::launch_attn_partial(a, stream); }),
+  const int rc = hip_status(timed(SPORK_KERNEL_ATTN, stream, [&] { return spork::launch_attn_partial(a, stream); }),
                   "spork_attn_decode (partial attention)");
   if (rc != SPORK_OK) return rc;
   return hip_status(timed(SPORK_KERNEL_MERGE, stream, [&] { return spork::launch_merge(a, stream); }),
