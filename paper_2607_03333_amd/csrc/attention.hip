@@ -58,9 +58,12 @@ __device__ __forceinline__ float softmax_step(float (&sv)[8], float& m, float& l
 // the slots read before it. Two kernels share that stream:
 //   narrow (attn_bf16): two workgroups per compute unit, up to 8 16-row tiles
 //     each, 16x16x32 products; decode and short verify rows, bound by HBM.
+//     With 8 waves: one workgroup per compute unit, up to 16 tiles; the
+//     multi-row shapes (long verify, prefill) while their units are short.
 //   wide (attn_bf16_wide): one workgroup per compute unit, up to 8 32-row
-//     tiles, 32x32x16 products; the multi-row shapes (long verify, prefill),
-//     where the matrix cores and the instruction issue bound a stage.
+//     tiles, 32x32x16 products; the multi-row shapes where the matrix cores
+//     and the instruction issue bound a stage and units are long enough
+//     (kWideStages) to pay for filling and draining its pipeline.
 //
 // LDS slot layout (1024 chunks of 16 bytes). Bank model (measured on
 // gfx950): 64 banks of 4 bytes, so a 16-byte slot s sits in bank group
@@ -437,11 +440,10 @@ struct Probs {
   }
 };
 
-template <int RTW, int BS>
-__global__ void __launch_bounds__(256, 2) attn_bf16(AttnArgs a) {
+template <int RTW, int BS, int NW>
+__global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) attn_bf16(AttnArgs a) {
   constexpr int D = 128;
-  constexpr int NW = 4;
-  constexpr int kRing = 4;
+  constexpr int kRing = NW == 4 ? 4 : 8;
   static_assert(BS == 16 || BS == 32, "unsupported block size");
   __shared__ uint4 smem[kRing][kStageChunks];
   __shared__ __align__(16) int tab[kUnitBlocks];
@@ -474,7 +476,7 @@ __global__ void __launch_bounds__(256, 2) attn_bf16(AttnArgs a) {
   // one): wave w of both shares SIMD w, and with 5-7 tiles (two for some
   // waves, one for others) the rotation pairs each wave holding two tiles
   // with one holding one.
-  const int cw = (wave + 2 * (static_cast<int>(blockIdx.x) / a.n_lists)) & 3;
+  const int cw = NW == 4 ? (wave + 2 * (static_cast<int>(blockIdx.x) / a.n_lists)) & 3 : wave;
   const int lane = tid & 63, r16 = lane & 15, g = lane >> 4;
   const uint16_t* __restrict__ qg = static_cast<const uint16_t*>(a.q);
   const int ntiles = (w.nrows + 15) >> 4;
@@ -1366,11 +1368,11 @@ __global__ void __launch_bounds__(256) counter_reset_kernel(int32_t* counters, i
 // --------------------------------------------------------------------------
 typedef void (*AttnKernel)(AttnArgs);
 
-template <int BS>
+template <int BS, int NW>
 AttnKernel pick_bf16(int row_tiles) {
-  switch ((row_tiles + 3) / 4) {
-    case 1: return attn_bf16<1, BS>;
-    case 2: return attn_bf16<2, BS>;
+  switch ((row_tiles + NW - 1) / NW) {
+    case 1: return attn_bf16<1, BS, NW>;
+    case 2: return attn_bf16<2, BS, NW>;
     default: return nullptr;
   }
 }
@@ -1387,10 +1389,11 @@ AttnKernel pick_f32(int rt) {
 }
 
 // Exactly the shapes attention_supported (dispatch_rules.cpp) accepts.
-AttnKernel pick_attention(int32_t dtype, int32_t d, int32_t bs, int32_t rt, int32_t waves) {
+AttnKernel pick_attention(int32_t dtype, int32_t d, int32_t bs, int32_t rt, int32_t waves, bool wide) {
   if (dtype == 1 && d == 128 && (waves == 4 || waves == 8)) {
-    if (bs == 16) return waves == 4 ? pick_bf16<16>(rt) : rt <= 16 ? attn_bf16_wide<16> : nullptr;
-    if (bs == 32) return waves == 4 ? pick_bf16<32>(rt) : rt <= 16 ? attn_bf16_wide<32> : nullptr;
+    if (waves == 8 && wide && rt <= 16) return bs == 16 ? attn_bf16_wide<16> : bs == 32 ? attn_bf16_wide<32> : nullptr;
+    if (bs == 16) return waves == 4 ? pick_bf16<16, 4>(rt) : pick_bf16<16, 8>(rt);
+    if (bs == 32) return waves == 4 ? pick_bf16<32, 4>(rt) : pick_bf16<32, 8>(rt);
   }
   if (dtype == 0) {
     if (d == 64 && bs == 16) return pick_f32<64, 16>(rt);
@@ -1404,7 +1407,7 @@ AttnKernel pick_attention(int32_t dtype, int32_t d, int32_t bs, int32_t rt, int3
 }  // namespace
 
 hipError_t launch_attn_partial(const AttnArgs& a, hipStream_t stream) {
-  AttnKernel k = pick_attention(a.dtype, a.head_dim, a.block_size, a.row_tiles, a.wg_waves);
+  AttnKernel k = pick_attention(a.dtype, a.head_dim, a.block_size, a.row_tiles, a.wg_waves, a.wide);
   if (k == nullptr) return hipErrorInvalidValue;
   const int threads = a.dtype == 1 ? 64 * a.wg_waves : 64;
   const int grid = a.dtype == 1 ? a.grid : a.grid + a.tail_units;

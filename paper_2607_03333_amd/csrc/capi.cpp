@@ -493,6 +493,7 @@ static int attention(const spork_plan* plan, const void* dev_image, const void* 
   a.n_out = p.n_out;
   a.row_tiles = p.row_tiles;
   a.wg_waves = p.shape.waves;
+  a.wide = p.wide;
   a.hq = sh.hq;
   a.hkv = sh.hkv;
   a.head_dim = sh.head_dim;

@@ -36,10 +36,11 @@ struct AttnArgs {
   const int32_t* wg_off;
   int32_t* cursors;
   int32_t n_units, grid, n_lists, n_out, row_tiles;
-  // waves of a bf16 workgroup: 4 (the narrow kernel, two persistent workgroups
-  // per compute unit, up to 8 16-row tiles each) or 8 (the wide kernel, one
-  // per compute unit, up to 16, a pair of them per wave)
+  // waves of a bf16 workgroup: 4 (two persistent workgroups per compute unit,
+  // up to 8 16-row tiles each) or 8 (one per compute unit, up to 16), and
+  // whether 8 waves run the wide kernel
   int32_t wg_waves;
+  bool wide;
   int32_t hq, hkv, head_dim, block_size, dtype;
   float scale_log2;  // sm_scale * log2(e): scores are kept in base 2
   const void* q;

@@ -25,6 +25,17 @@ struct Range {
 constexpr int64_t kStageWeight8[5] = {0, 572, 722, 821, 1024};
 int64_t stage_weight8(int32_t slice_tiles) { return kStageWeight8[std::min(4, (slice_tiles + 3) / 4)]; }
 
+// The wide kernel runs an 8-wave plan whose units cost this many full stages on
+// average and whose stages are full ones (13 to 16 tiles) but for a sixteenth
+// of their cost: it does a full stage faster, an emptier one more slowly (its
+// tiles have 32 rows), and takes about 2 us longer to start and end a unit.
+// Wide against 16-row tiles, 32 sessions of 32,000 tokens: 64/8 heads, 24 drafts
+// (13 tiles) 1,020 against 1,059 us, a 30-row probe prefill (16) 1,087 against
+// 1,156, 17 drafts (9) 899 against 875, 40 drafts (12 + 9) 1,840 against 1,827.
+// 64/8 heads, 4 sessions of 8,000 tokens, the prefill (23 full stages a unit):
+// 70.9 against 62.3; 16 of 300 tokens, 24 drafts (5): 43.4 against 39.6.
+constexpr int64_t kWideStages = 48;
+
 struct Unit {  // one token segment of one item, split over `slices` row slices
   int32_t item, lo, hi, slices;
   int64_t cost() const { return static_cast<int64_t>(hi - lo) * slices; }
@@ -422,6 +433,13 @@ std::string build_plan(const BlockManager& bm, const PlanShape& shape, const int
       level += std::max<int64_t>(kTileTokens * wunit, (overflow + lanes - 1) / lanes);
     }
     lists.swap(best);
+    if (shape.waves == 8) {
+      int64_t units = 0, slice_tokens = 0;
+      for (const auto& l : lists) units += static_cast<int64_t>(l.size());
+      for (size_t it = 0; it < items.size(); ++it)
+        slice_tokens += static_cast<int64_t>(item_range[it]->hi - item_range[it]->lo) * slices_of[it];
+      p.wide = tokens >= kWideStages * kTileTokens * wunit * units && tokens * 16 >= slice_tokens * wunit * 15;
+    }
     wg_off.push_back(0);
     for (auto& l : lists) {
       // longest unit first; the row slices of a piece stay adjacent

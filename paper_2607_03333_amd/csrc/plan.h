@@ -33,6 +33,7 @@ struct Plan {
   int32_t n_threads = 0, n_rows = 0, n_groups = 0, n_items = 0;
   int32_t n_units = 0, grid = 0, n_partials = 0, row_tiles = 1, n_out = 0;
   int32_t n_lists = 0;  // unit lists (persistent launch: one per compute unit)
+  bool wide = false;    // 8-wave plans: the wide kernel runs the units (else 16-row tiles)
   int32_t max_range_tiles = 0;  // 16-row tiles of the largest range's row set, before slicing
   int64_t shared_tokens = 0, private_tokens = 0, flat_tokens = 0;
   // device image: sections at 256-byte aligned byte offsets

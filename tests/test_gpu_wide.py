@@ -1,13 +1,16 @@
-"""The wide attention kernel (ranges of more than 8 row tiles) where its loop
-can go wrong: one to many 32-token stages (a single stage, the first and last
+"""The 8-wave attention kernels (ranges of more than 8 row tiles), 16-row tiles
+for short units and the wide kernel for long ones, where their loops can go
+wrong: one to many 32-token stages (a single stage, the first and last
 pairs, the ring's depth and one past it), row counts that end inside and on a
 32-row tile and on a full slice, both block sizes, and scores that grow along
 the context so that the softmax reference moves in every stage. Tolerances
 are the parity tests' (bf16 results, gpu_cases)."""
+import functools
+
 import numpy as np
 import pytest
 
-from paper_2607_03333_amd import synth
+from paper_2607_03333_amd import runner, synth
 from gpu_cases import run_workload
 
 pytestmark = pytest.mark.gpu
@@ -58,4 +61,24 @@ def test_wide_reference_moves_in_every_stage():
     wl.steps[0].q = synth.f32_to_bf16_bits(np.abs(q))
     halve_v(wl)
     dw = run_workload(wl, "wide growing scores")
+    dw.close()
+
+
+@pytest.mark.parametrize("block_size", [16, 32])
+@pytest.mark.parametrize("k,prefix,gain", [
+    (24, 1700, 1.0),   # 200 rows: six whole 32-row tiles and 8 rows; 1,725 tokens
+    (27, 1764, 4.0),   # 224 rows: seven whole tiles; 1,792 tokens: 56 whole stages
+    (31, 1793, 1.0),   # 256 rows, a full slice; 1,825 tokens: an odd number of stages, one token in the last
+    (62, 1600, 12.0),  # 504 rows in two slices, a sharp softmax
+])
+def test_wide_long_units(monkeypatch, k, prefix, gain, block_size):
+    """Planned for one compute unit, a unit is a whole range: more than 48
+    stages of 13 to 16 row tiles, which the wide kernel runs."""
+    monkeypatch.setattr(runner, "DeviceWorkload", functools.partial(runner.DeviceWorkload, n_cu=1))
+    wl = synth.make(3, sessions=1, prefix=prefix, vocab=333, verify_k=k, block_size=block_size, q_gain=gain)
+    if gain > 1:
+        halve_v(wl)
+    dw = run_workload(wl, f"wide long K={k} prefix={prefix} bs={block_size}")
+    info = dw.steps[0].info
+    assert info["attn_waves"] == 8 and info["max_row_tiles"] >= 13
     dw.close()

@@ -135,6 +135,6 @@ def test_attention_kernels_leave_reads_in_flight_alone(tmp_path):
             name = None
         elif name:
             kernels[name].append(t)
-    assert len(kernels) == 6  # narrow (one and two row tiles per wave) and wide, 16- and 32-token blocks
+    assert len(kernels) == 10  # narrow (4 and 8 waves, one and two row tiles per wave) and wide, 16- and 32-token blocks
     for name, lines in kernels.items():
         assert pending_read_uses(lines) == [], name
