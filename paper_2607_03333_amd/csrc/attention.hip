@@ -760,6 +760,9 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) attn_bf16(AttnArgs a
 // matrix cores busy 35 to 43% and 40 to 50%), but the chip runs these steps at
 // its power limit and lowers the clock as the cycles get denser (2.19 to 1.97
 // and 1.94 to 1.74 GHz).
+// The narrow kernel with 8 waves (scalar block bases, lighter softmax) runs those
+// three batches as fast; this one is ahead where slices are full (see
+// kWideStages in plan.cpp).
 // --------------------------------------------------------------------------
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
