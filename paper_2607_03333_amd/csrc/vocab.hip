@@ -31,17 +31,24 @@ __global__ void __launch_bounds__(64) accept_kernel(AcceptArgs a) { accept_unit(
 // the span's rows after its first, its exponential (1 for an empty set) and
 // the gate. Span offsets are clamped to [0, n_rows]; a reversed span is empty.
 // --------------------------------------------------------------------------
-// Threads of a confidence workgroup. The pass has 2048 to 4095 (row, chunk)
-// units where rows are few; at 128 threads the chip holds 4096 of them at
-// once, at 256 threads 2048 and the few left over ran alone at the end.
-constexpr int kConfThreads = 128;
+// A confidence workgroup has 256 threads where there are few units, so that
+// each has its loads in flight at once, or where long units fill one and a half
+// rounds of the chip or so; else 128, so that a few units more than the chip
+// holds at 256 don't run alone at the end. 256 against 128 threads (us, on
+// cold caches): 20 rows of 151,936 fp32 logits, 360 units, 13.5 and 14.2; 64
+// rows of 32,000 bf16, 192 units, 11.0 and 12.3. Calls back to back: 500 rows
+// of 151,936 fp32, 2,500 units, 51.3 and 57.7; 1,365 bf16 rows, 2,730 units,
+// 68.6 and 76.5. On the other side: 114 bf16 rows, 2,052 units, 14.3 and 13.0;
+// 1,081, 2,162 units, 59.8 and 58.2; 1,200 rows of 32,000, 2,400 units of 32
+// KB, 21.0 and 19.1; 2,000 fp32 rows of 32,000, 4,000 units, 45.6 and 43.3.
+constexpr int64_t kConfFew = 768, kConfRound = 2304, kConfRounds = 3584, kConfShort = 32 << 10;
 
-template <typename T>
-__global__ void __launch_bounds__(kConfThreads) conf_chunks(ConfArgs a) {
+template <typename T, int NT>
+__global__ void __launch_bounds__(NT) conf_chunks(ConfArgs a) {
   const int row = blockIdx.x / a.chunks, c = blockIdx.x % a.chunks;
   const size_t u = static_cast<size_t>(row) * a.chunks + c;
-  argmax_unit<T, kConfThreads, true>(static_cast<const T*>(a.logits) + static_cast<size_t>(row) * a.vocab, a.vocab, a.chunks,
-                            c, a.keys + u, reinterpret_cast<float2*>(a.ms) + u);
+  argmax_unit<T, NT, true>(static_cast<const T*>(a.logits) + static_cast<size_t>(row) * a.vocab, a.vocab, a.chunks, c,
+                           a.keys + u, reinterpret_cast<float2*>(a.ms) + u);
 }
 
 __device__ __forceinline__ float row_logprob(const ConfArgs& a, int row, int* greedy) {
@@ -102,10 +109,12 @@ hipError_t launch_argmax(const AcceptArgs& a, hipStream_t stream) {
 
 hipError_t launch_conf_chunks(const ConfArgs& a, hipStream_t stream) {
   if (a.n_rows == 0) return hipSuccess;
-  if (a.logits_dtype == 1)
-    hipLaunchKernelGGL(conf_chunks<uint16_t>, dim3(a.n_rows * a.chunks), dim3(kConfThreads), 0, stream, a);
-  else
-    hipLaunchKernelGGL(conf_chunks<float>, dim3(a.n_rows * a.chunks), dim3(kConfThreads), 0, stream, a);
+  const int64_t units = static_cast<int64_t>(a.n_rows) * a.chunks;
+  const int64_t unit_bytes = static_cast<int64_t>(a.vocab) * (a.logits_dtype == 1 ? 2 : 4) / a.chunks;
+  const bool wide = units <= kConfFew || (units > kConfRound && units < kConfRounds && unit_bytes > kConfShort);
+  const auto kernel = a.logits_dtype == 1 ? (wide ? conf_chunks<uint16_t, 256> : conf_chunks<uint16_t, 128>)
+                                          : (wide ? conf_chunks<float, 256> : conf_chunks<float, 128>);
+  hipLaunchKernelGGL(kernel, dim3(a.n_rows * a.chunks), dim3(wide ? 256 : 128), 0, stream, a);
   return hipGetLastError();
 }
 

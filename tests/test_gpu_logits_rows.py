@@ -11,7 +11,7 @@ import torch
 import oracle
 from paper_2607_03333_amd import runner, spork, synth
 from gpu_cases import run_workload, say
-from test_gpu_confidence import LOGPROB_TOL
+from test_gpu_confidence import LOGPROB_TOL, check as check_confidence
 
 pytestmark = pytest.mark.gpu
 _DT = {synth.BF16: spork.SPORK_DTYPE_BF16, synth.F32: spork.SPORK_DTYPE_F32}
@@ -119,3 +119,17 @@ def test_a_vocabulary_that_does_not_fill_vectors_costs_about_the_same():
     say(f"  us at 151,936 and 151,935: confidence and fp32 verify {times}")
     for aligned, other in zip(times[151936], times[151935]):
         assert other <= 1.5 * aligned
+
+
+@pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
+@pytest.mark.parametrize("rows,vocab", [(768, 515), (769, 515), (2304, 515), (2305, 515), (2305, 8192), (2305, 16400),
+                                        (3583, 16392), (3584, 16392)])
+def test_confidence_workgroup_sizes(dtype, rows, vocab):
+    """Both sides of every line between 128 and 256 threads: by the number of
+    units (768, 2,304, 3,584) and by a unit's length (32 KB)."""
+    rng = np.random.default_rng(rows)
+    x = rng.standard_normal((rows, vocab)).astype(np.float32)
+    x[np.arange(rows), rng.integers(0, vocab, rows)] = 7.0
+    st = synth.to_storage(x, dtype)
+    say(f"confidence {dtype} rows={rows} V={vocab}")
+    check_confidence(st, dtype, np.array([0, 5, rows // 2, rows]), tag=f"{dtype} rows={rows} V={vocab}")
