@@ -6,12 +6,23 @@ namespace spork {
 namespace {
 
 // Fewest (token, KV head) pairs of a call that goes a block at a time. Below,
-// the scatter by token has more threads to hide the stores' latency with (bf16,
-// 128 channels, 512 tokens of 512 sequences, 8 heads: 7.4 us against 8.0; 272
-// tokens in runs of 17: 5.3 against 4.9; 816 tokens, 4 heads: both 5.4). Above,
-// the 2-byte stores bound it (8 heads: 576 tokens in runs of 9: 8.0 us against
-// 6.2; 1600 single tokens: 27.9 against 15.5; 4000 in a row: 35.4 against 9.3).
+// the scatter by token has more threads to hide the stores' latency with; above,
+// its 2- and 4-byte stores bound it. By token against by blocks, calls back to
+// back, 8 heads of 128 channels (us): bf16, 16-token blocks, 2,048 tokens in runs
+// of 9 21.9 and 8.3, in a row 18.3 and 8.2, each in a block of its own 31.2 and
+// 18.0; fp32 35.9 and 10.1, 25.1 and 8.3, 36.5 and 30.8. At the line itself (576
+// tokens) the two are level in 16-token blocks (8.0 and 8.1 in runs of 9); in
+// 32-token blocks tokens that each have a block to themselves pay for the line
+// being there: bf16 10.2 and 10.8, fp32 9.9 and 10.9, and 1,024 of 64 bf16
+// channels 8.6 and 9.7, where runs of 9 gain (2,048: 23.3 and 8.6).
 constexpr int64_t kBlocksMin = 4608;
+// Most waves of a launch with several waves per block: while there is room for
+// them, they store what one wave would store alone, in a row. 576 single bf16
+// tokens in 32-token blocks, one wave and four: 14.4 and 10.8 us; 576 in runs of
+// 9 on cold caches 13.2 and 9.7. Past it the chip is full either way, and more
+// waves only make its last round longer (15,001 tokens in a row, 4 heads, one
+// wave of 3,752 and two: 10.6 and 13.2 us).
+constexpr int64_t kSharedWaves = 2048;
 
 // Scatter by token: a thread per 16-byte chunk of a token and head.
 template <typename T>
@@ -41,10 +52,10 @@ __global__ void __launch_bounds__(256) kv_write_kernel(int hkv, int D, int BS, i
 }
 
 // --------------------------------------------------------------------------
-// The scatter of many tokens, a block at a time: one wave per (window of BS
-// tokens, KV head). The V pool holds a block transposed ([D][BS]), so a token's
+// The scatter of many tokens, a block at a time: a workgroup of one wave, or of
+// several (kSharedWaves), per (window of BS tokens, KV head). The V pool holds a block transposed ([D][BS]), so a token's
 // channels lie BS elements apart and the kernel above stores them one by one;
-// here the wave transposes its window through LDS, and a window whose tokens
+// here the workgroup transposes its window through LDS, and a window whose tokens
 // fill one block in order (all but the ends of an appended run) goes out as
 // contiguous 16-byte stores. The windows are laid out from the offset of the
 // first token in its block. Any other window stores V by element, tokens
@@ -54,20 +65,22 @@ __global__ void __launch_bounds__(256) kv_write_kernel(int hkv, int D, int BS, i
 // of four rows; the padding puts the pieces that a wave reads at once into
 // different banks (fp32 with 32-token blocks: two lanes per bank).
 // Bound by the stream from and to HBM: 15,001 tokens of 8 heads of 128 bf16
-// channels 149 us by element stores, 38.8 us by blocks, 23.6 us (5.2 TB/s)
-// with non-temporal loads, which leave the caches to the stores. Non-temporal
-// stores too: 21.9 us, but the attention that follows reads the blocks.
+// channels 149 us by element stores, 38.8 us by blocks, 23.6 us with
+// non-temporal loads, which leave the caches to the stores (calls back to back,
+// whose 123 MB the last-level cache partly holds; cold 25.9 us, 4.7 TB/s).
+// Non-temporal stores too: 21.9 us, but the attention that follows reads the
+// blocks.
 // --------------------------------------------------------------------------
-template <typename T, int D, int BS>
-__global__ void __launch_bounds__(64) kv_write_blocks(int hkv, int64_t num_slots, T* kc, T* vc, const int64_t* slots,
+template <typename T, int D, int BS, int NT>
+__global__ void __launch_bounds__(NT) kv_write_blocks(int hkv, int64_t num_slots, T* kc, T* vc, const int64_t* slots,
                                                       const T* kn, const T* vn, int n, int* bad) {
   constexpr int VEC = 16 / sizeof(T), CH = D / VEC;  // 16-byte chunks of a token
   constexpr int PACK = 4 / sizeof(T);                // tokens of an LDS row
   constexpr int R = BS / PACK, QN = R / 4;           // rows; pieces per channel
   constexpr int STRIDE = D + (QN == 2 ? 8 : 4);
-  constexpr int KIT = BS * CH / 64, VIT = R * CH / 64, OIT = D * QN / 64;
-  __shared__ uint32_t tile[R * STRIDE];
-  const int lane = threadIdx.x;
+  constexpr int KIT = BS * CH / NT, VIT = R * CH / NT, OIT = D * QN / NT;
+  __shared__ __align__(16) uint32_t tile[R * STRIDE];
+  const int tid = threadIdx.x;
   const int h = static_cast<int>(blockIdx.x % static_cast<unsigned>(hkv));
   const int64_t s0 = slots[0];
   const int shift = s0 < 0 ? 0 : static_cast<int>(s0 % BS);
@@ -81,23 +94,23 @@ __global__ void __launch_bounds__(64) kv_write_blocks(int hkv, int64_t num_slots
   uint4 vr[VIT][PACK], kr[KIT];
 #pragma unroll
   for (int it = 0; it < VIT; ++it) {
-    const int r = (it * 64 + lane) / CH, c = lane % CH;
+    const int r = (it * NT + tid) / CH, c = tid % CH;
 #pragma unroll
     for (int p = 0; p < PACK; ++p) vr[it][p] = has(r * PACK + p) ? load_stream(src(vn, r * PACK + p, c)) : zero;
   }
 #pragma unroll
   for (int it = 0; it < KIT; ++it) {
-    const int t = (it * 64 + lane) / CH;
-    kr[it] = has(t) ? load_stream(src(kn, t, lane % CH)) : zero;
+    const int t = (it * NT + tid) / CH;
+    kr[it] = has(t) ? load_stream(src(kn, t, tid % CH)) : zero;
   }
-  // lane t (and t + BS, ...): the slot of token t
-  const int tt = lane % BS;
+  // lane t of each wave (and t + BS, ...): the slot of token t
+  const int tt = tid % BS;
   const int64_t slot = has(tt) ? slots[i0 + tt] : -1;
   const bool ok = slot >= 0 && slot < num_slots;
-  if (bad != nullptr && h == 0 && lane < BS && has(tt) && !ok) atomicAdd(bad, 1);
+  if (bad != nullptr && h == 0 && tid < BS && has(tt) && !ok) atomicAdd(bad, 1);
 #pragma unroll
   for (int it = 0; it < VIT; ++it) {
-    const int r = (it * 64 + lane) / CH, c = lane % CH;
+    const int r = (it * NT + tid) / CH, c = tid % CH;
     uint32_t* row = tile + r * STRIDE + c * VEC;
     if constexpr (PACK == 1) {
       *reinterpret_cast<uint4*>(row) = vr[it][0];
@@ -117,27 +130,27 @@ __global__ void __launch_bounds__(64) kv_write_blocks(int hkv, int64_t num_slots
     uint4* kd = reinterpret_cast<uint4*>(kc + base);
     uint4* vd = reinterpret_cast<uint4*>(vc + base);
 #pragma unroll
-    for (int it = 0; it < KIT; ++it) kd[it * 64 + lane] = kr[it];
+    for (int it = 0; it < KIT; ++it) kd[it * NT + tid] = kr[it];
 #pragma unroll
     for (int it = 0; it < OIT; ++it) {
-      const int d = (it * 64 + lane) / QN, q = lane % QN;
+      const int d = (it * NT + tid) / QN, q = tid % QN;
       const uint32_t* col = tile + 4 * q * STRIDE + d;
-      vd[it * 64 + lane] = make_uint4(col[0], col[STRIDE], col[2 * STRIDE], col[3 * STRIDE]);
+      vd[it * NT + tid] = make_uint4(col[0], col[STRIDE], col[2 * STRIDE], col[3 * STRIDE]);
     }
     return;
   }
 #pragma unroll
   for (int it = 0; it < KIT; ++it) {
-    const int64_t ks = __shfl(slot, (it * 64 + lane) / CH);
+    const int64_t ks = __shfl(slot, (it * NT + tid) / CH);
     if (ks >= 0 && ks < num_slots)
-      *reinterpret_cast<uint4*>(kc + ((static_cast<size_t>(ks / BS) * hkv + h) * BS + ks % BS) * D + lane % CH * VEC) =
+      *reinterpret_cast<uint4*>(kc + ((static_cast<size_t>(ks / BS) * hkv + h) * BS + ks % BS) * D + tid % CH * VEC) =
           kr[it];
   }
   if (!ok) return;
   T* vd = vc + (static_cast<size_t>(slot / BS) * hkv + h) * (D * BS) + slot % BS;
   const T* col = reinterpret_cast<const T*>(tile + tt / PACK * STRIDE) + tt % PACK;
 #pragma unroll 8
-  for (int d = lane / BS; d < D; d += 64 / BS) vd[static_cast<size_t>(d) * BS] = col[d * PACK];
+  for (int d = tid / BS; d < D; d += NT / BS) vd[static_cast<size_t>(d) * BS] = col[d * PACK];
 }
 
 template <typename T>
@@ -162,14 +175,28 @@ __global__ void __launch_bounds__(256) image_patch_kernel(int32_t* image, ImageP
   for (int i = threadIdx.x; i < patch.n; i += 256) image[patch.off[i]] = patch.val[i];
 }
 
+template <typename T, int D, int BS>
+void write_blocks(int hkv, int64_t num_slots, T* kc, T* vc, const int64_t* slots, const T* kn, const T* vn, int n, int* bad,
+                  hipStream_t stream) {
+  constexpr int kPieces = D * BS * sizeof(T) / 16 * sizeof(T) / 4;  // of the window's LDS rows, one loaded by a thread at a time
+  constexpr int kShared = kPieces < 256 ? kPieces : 256;
+  // one window more than n / BS rounded up: the first may hold a single token
+  const unsigned units = static_cast<unsigned>((static_cast<int64_t>(n) + 2 * BS - 2) / BS * hkv);
+  if (static_cast<int64_t>(units) * (kShared / 64) <= kSharedWaves)
+    hipLaunchKernelGGL((kv_write_blocks<T, D, BS, kShared>), dim3(units), dim3(kShared), 0, stream, hkv, num_slots, kc, vc,
+                       slots, kn, vn, n, bad);
+  else
+    hipLaunchKernelGGL((kv_write_blocks<T, D, BS, 64>), dim3(units), dim3(64), 0, stream, hkv, num_slots, kc, vc, slots, kn,
+                       vn, n, bad);
+}
+
 template <typename T>
-void write_blocks(int hkv, int d, int bs, int64_t num_slots, T* kc, T* vc, const int64_t* slots, const T* kn,
-                  const T* vn, int n, int* bad, hipStream_t stream) {
-  // one window more than n / bs rounded up: the first may hold a single token
-  const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(n) + 2 * bs - 2) / bs * hkv));
-  auto* k = d == 128 ? (bs == 16 ? kv_write_blocks<T, 128, 16> : kv_write_blocks<T, 128, 32>)
-                     : (bs == 16 ? kv_write_blocks<T, 64, 16> : kv_write_blocks<T, 64, 32>);
-  hipLaunchKernelGGL(k, grid, dim3(64), 0, stream, hkv, num_slots, kc, vc, slots, kn, vn, n, bad);
+void write_blocks(int hkv, int d, int bs, int64_t num_slots, void* kc, void* vc, const int64_t* slots, const void* kn,
+                  const void* vn, int n, int* bad, hipStream_t stream) {
+  const auto f = d == 128 ? (bs == 16 ? write_blocks<T, 128, 16> : write_blocks<T, 128, 32>)
+                          : (bs == 16 ? write_blocks<T, 64, 16> : write_blocks<T, 64, 32>);
+  f(hkv, num_slots, static_cast<T*>(kc), static_cast<T*>(vc), slots, static_cast<const T*>(kn), static_cast<const T*>(vn),
+    n, bad, stream);
 }
 
 }  // namespace
@@ -186,13 +213,8 @@ hipError_t launch_kv_write(int32_t dtype, int32_t hkv, int32_t head_dim, int32_t
                            hipStream_t stream) {
   if (n == 0) return hipSuccess;
   if (static_cast<int64_t>(n) * hkv >= kBlocksMin && (head_dim == 64 || head_dim == 128) && (block_size == 16 || block_size == 32)) {
-    if (dtype == 1)
-      write_blocks(hkv, head_dim, block_size, num_slots, static_cast<uint16_t*>(k_cache),
-                   static_cast<uint16_t*>(v_cache), slots, static_cast<const uint16_t*>(k_new),
-                   static_cast<const uint16_t*>(v_new), n, bad_slots, stream);
-    else
-      write_blocks(hkv, head_dim, block_size, num_slots, static_cast<float*>(k_cache), static_cast<float*>(v_cache),
-                   slots, static_cast<const float*>(k_new), static_cast<const float*>(v_new), n, bad_slots, stream);
+    const auto f = dtype == 1 ? write_blocks<uint16_t> : write_blocks<float>;
+    f(hkv, head_dim, block_size, num_slots, k_cache, v_cache, slots, k_new, v_new, n, bad_slots, stream);
     return hipGetLastError();
   }
   const int vec = dtype == 1 ? 8 : 4;
