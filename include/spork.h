@@ -149,7 +149,7 @@ typedef struct spork_shape {
   int32_t head_dim;   /* D */
   int32_t block_size; /* tokens per block */
   int32_t dtype;      /* SPORK_DTYPE_*: element type of q, K/V pools and out */
-  float sm_scale;     /* softmax scale applied to q.k */
+  float sm_scale;     /* softmax scale applied to q.k: any finite value */
 } spork_shape;
 
 /* Write n tokens' K and V into the pools.

@@ -403,10 +403,9 @@ __device__ __forceinline__ void argmax_tail(const AttnArgs& a, int tid, int& nex
 template <int XOR0, int N, int NA, typename Acc, typename Pop>
 __device__ __forceinline__ void rescale(const float (&sv)[N], float c, float& m, float& l, Acc (&o)[NA], float& ps,
                                         Pop& pop) {
-  float mx = sv[0];
+  float mx = sv[0] * c;
 #pragma unroll
-  for (int e = 1; e < N; ++e) mx = fmaxf(mx, sv[e]);
-  mx *= c;
+  for (int e = 1; e < N; ++e) mx = fmaxf(mx, sv[e] * c);
 #pragma unroll
   for (int x = XOR0; x < 64; x *= 2) mx = fmaxf(mx, __shfl_xor(mx, x));
   if (mx > m + kRescaleSlack) {  // row-uniform: all lanes of the row agree
@@ -425,6 +424,10 @@ __device__ __forceinline__ void rescale(const float (&sv)[N], float c, float& m,
     pop.set(e, pv);
   }
 }
+
+// The score of a masked position: -inf once times the scores' factor (which is
+// not zero, but may be below it).
+__device__ __forceinline__ float masked_score(float c) { return c < 0.0f ? -kNegInf : kNegInf; }
 
 // Probabilities as packed bf16 pairs, the B operand of the P.V products.
 template <int N>
@@ -547,7 +550,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) attn_bf16(AttnArgs a
   }
   const uint32_t vaddr = smem_base + 16u * (BS == 16 ? 512 + 256 * (g >> 1) + 2 * r16 + (g & 1)
                                                      : 512 + 4 * r16 + (g ^ v_swz<32, false>(r16)));
-  const float c = a.scale_log2;
+  const float c = a.scale_log2, masked = masked_score(c);
   auto read_k = [&](u32x4 (&kr)[8], int st) __attribute__((always_inline)) {
     const uint32_t soff = static_cast<uint32_t>(st % kRing) * (kStageChunks * 16);
 #pragma unroll
@@ -604,7 +607,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) attn_bf16(AttnArgs a
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const int tk = tb + 8 * g + e;
-          if (tk < w.tok_lo || tk >= tok_hi || tk > hz[j]) sv[e] = kNegInf;
+          if (tk < w.tok_lo || tk >= tok_hi || tk > hz[j]) sv[e] = masked;
         }
       }
 #pragma unroll
@@ -837,7 +840,7 @@ __global__ void __launch_bounds__(512, 1) attn_bf16_wide(AttnArgs a) {
       vaddr[h] = smem_base + 16u * (BS == 16 ? 512 + 256 * h + 2 * r32 + (g ^ v_swz<16, true>(r32))
                                              : 512 + 4 * r32 + ((2 * h + g) ^ v_swz<32, true>(r32)));
   }
-  const float c = a.scale_log2;
+  const float c = a.scale_log2, masked = masked_score(c);
   auto slot_off = [&](int st) __attribute__((always_inline)) {
     return static_cast<uint32_t>(st % kRing) * (kStageChunks * 16);
   };
@@ -937,7 +940,7 @@ __global__ void __launch_bounds__(512, 1) attn_bf16_wide(AttnArgs a) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int pos = 16 * (e >> 3) + (e & 7);
-          sv[e] = pos < lo || pos > hi ? kNegInf : sv[e];
+          sv[e] = pos < lo || pos > hi ? masked : sv[e];
         }
       }
       const float nm = -m;

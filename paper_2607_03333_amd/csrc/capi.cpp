@@ -3,6 +3,7 @@
 #include "spork.h"
 
 #include <algorithm>
+#include <cfloat>
 #include <climits>
 #include <cmath>
 #include <cstring>
@@ -500,6 +501,10 @@ static int attention(const spork_plan* plan, const void* dev_image, const void* 
   a.block_size = sh.block_size;
   a.dtype = sh.dtype;
   a.scale_log2 = sh.sm_scale * 1.4426950408889634f;
+  // The bf16 kernels mask a score by an infinity before the scale: a scale of
+  // zero stands in as the smallest normal number, whose products with any score
+  // are zero to the exponential.
+  if (sh.dtype == SPORK_DTYPE_BF16 && a.scale_log2 == 0.0f) a.scale_log2 = FLT_MIN;
   a.q = q;
   a.k_cache = k_cache;
   a.v_cache = v_cache;
