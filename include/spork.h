@@ -189,6 +189,8 @@ typedef struct spork_plan_info {
   int32_t attn_waves;      /* waves per attention workgroup (bf16: 4, two workgroups per
                               compute unit, or 8 when a range has more than 8 row tiles,
                               one per compute unit; fp32: 1) */
+  int32_t attn_wide;       /* 1: the 8 waves run the wide kernel (32-row tiles), 0: 16-row
+                              tiles */
   size_t control_bytes;    /* leading workspace bytes that hold control words (see
                               spork_workspace_clear) */
 } spork_plan_info;

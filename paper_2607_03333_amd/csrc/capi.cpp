@@ -6,6 +6,7 @@
 #include <cfloat>
 #include <climits>
 #include <cmath>
+#include <cstddef>
 #include <cstring>
 #include <exception>
 #include <new>
@@ -19,6 +20,10 @@
 #include "noalloc.h"
 #include "vocab_kernels.h"
 #include "plan.h"
+
+// attn_wide lies in what was padding: offsets and size are those of callers
+// built before it.
+static_assert(offsetof(spork_plan_info, control_bytes) == 88 && sizeof(spork_plan_info) == 96, "spork_plan_info layout");
 
 struct spork_cache {
   spork::BlockManager bm;
@@ -340,6 +345,7 @@ int spork_plan_get_info(const spork_plan* plan, spork_plan_info* info) {
   info->n_partials = p.n_partials;
   info->max_row_tiles = p.row_tiles;
   info->attn_waves = p.shape.waves;
+  info->attn_wide = p.wide ? 1 : 0;
   info->image_bytes = p.image.size();
   info->workspace_bytes = p.workspace_bytes;
   info->shared_tokens = p.shared_tokens;

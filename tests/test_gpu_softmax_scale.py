@@ -27,5 +27,6 @@ def test_scales_up_to_zero(monkeypatch, kernel, make, scale):
     wl = make()
     wl.sm_scale = scale
     dw = run_workload(wl, f"{kernel} scale {scale}")
-    assert dw.steps[-1].info["attn_waves"] == {"f": 1, "4": 4}.get(kernel[0], 8)
+    info = dw.steps[-1].info
+    assert info["attn_waves"] == {"f": 1, "4": 4}.get(kernel[0], 8) and info["attn_wide"] == int("wide" in kernel)
     dw.close()
