@@ -466,11 +466,6 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) attn_bf16(AttnArgs a
   const int taken = __builtin_amdgcn_readfirstlane(next_unit);
   if (taken < 0 || taken >= list_len) break;
   const WaveDesc w = load_wave_desc(a.waves + list0 + taken);
-  if (w.item < 0) {  // padding (not emitted on persistent lists): every wave reads next_unit first
-    barrier_nofence();
-    if (tid == 0) next_unit = atomicAdd(a.cursors + list * kCursorStride, 1);
-    continue;
-  }
   const UnitStart u = unit_start<BS>(a, w);
   const int tok_hi = u.tok_hi, tb0 = u.tb0, nstage = u.nstage;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
@@ -790,11 +785,6 @@ __global__ void __launch_bounds__(512, 1) attn_bf16_wide(AttnArgs a) {
   const int taken = __builtin_amdgcn_readfirstlane(next_unit);
   if (taken < 0 || taken >= list_len) break;
   const WaveDesc w = load_wave_desc(a.waves + list0 + taken);
-  if (w.item < 0) {
-    barrier_nofence();
-    if (tid == 0) next_unit = atomicAdd(a.cursors + list * kCursorStride, 1);
-    continue;
-  }
   const UnitStart u = unit_start<BS>(a, w);
   const int tok_hi = u.tok_hi, tb0 = u.tb0, nstage = u.nstage;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

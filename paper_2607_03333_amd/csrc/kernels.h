@@ -18,10 +18,6 @@ struct AcceptArgs {
   int32_t* next_token;
   int32_t* argmax_out;
   uint64_t* keys;  // [rows][chunks] workspace
-  // nullable: int32 counters of the attention launch that follows, which the
-  // argmax launch clears
-  int32_t* counters;
-  int32_t n_counters;
 };
 
 struct AttnArgs {
@@ -55,9 +51,9 @@ struct AttnArgs {
   float* part_ml;  // [n_partials][2] running max (base 2) and sum
   // Verify step: accept units appended to the merge grid (acc.n_verify of them).
   AcceptArgs acc;
-  // Argmax units (row x vocabulary chunk) the persistent bf16 launch works
-  // through after its lists, through cursors[n_lists]; 0 when the argmax has
-  // a launch of its own.
+  // Argmax units (row x vocabulary chunk) of a verify step, 0 else: the
+  // persistent bf16 launch works through them after its lists, through
+  // cursors[n_lists]; the fp32 launch has a workgroup for each behind its own.
   int32_t tail_units;
   // Cursors the merge launch returns to zero for the next call (the
   // persistent launch's n_lists + 1; 0 otherwise).

@@ -13,8 +13,6 @@ namespace {
 
 template <typename T>
 __global__ void __launch_bounds__(256) argmax_chunks(AcceptArgs a) {
-  if (a.counters != nullptr)
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < a.n_counters; i += gridDim.x * 256) a.counters[i] = 0;
   const int row = blockIdx.x / a.chunks, c = blockIdx.x % a.chunks;
   argmax_unit<T, 256, false>(static_cast<const T*>(a.logits) + static_cast<size_t>(row) * a.vocab, a.vocab, a.chunks,
                              c, a.keys + static_cast<size_t>(row) * a.chunks + c, nullptr);
