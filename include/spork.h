@@ -284,11 +284,11 @@ int spork_verify_workspace_bytes(int32_t n_verify, int32_t k_drafts, int32_t voc
  * offset) by spork_verify_workspace_bytes; ws_bytes covers both. With a
  * plan the workspace's control words must be zero on entry
  * (spork_workspace_clear).
- * With a bf16 plan the step is two launches on `stream`: the partial
- * attention, whose persistent workgroups take the argmax units once their
- * own lists are done, then the merge together with the accept (and the
- * cursor clear). fp32 plan: the argmax, the partial attention, the merge
- * with the accept. Without a plan: the argmax, then the accept. */
+ * With a plan the step is two launches on `stream`: the partial attention
+ * with the argmax (bf16: persistent workgroups take the argmax units once
+ * their own lists are done; fp32: workgroups of their own), then the merge
+ * together with the accept (and the cursor clear). Without a plan: the
+ * argmax, then the accept. */
 int spork_verify_accept(const spork_plan* plan, const void* dev_image, const void* q,
                         const void* k_cache, const void* v_cache, void* out, float* lse,
                         const void* logits, int32_t logits_dtype, int32_t vocab,
@@ -371,9 +371,10 @@ int spork_ngram_workspace_bytes(int32_t n_seqs, int64_t max_len, size_t* bytes);
  * sequence expected); longer sequences are still scanned whole, more slowly.
  * workspace (device, 256-byte aligned, ws_bytes >= the size from
  * spork_ngram_workspace_bytes; any contents on entry).
- * Two launches on `stream`. SPORK_E_INVAL for bad sizes (1 <= n_min <=
- * n_max <= 32, 0 <= k <= 4096, 0 <= max_len < 2^31) or a NULL required
- * pointer, SPORK_E_CAPACITY for a short workspace. */
+ * Two launches on `stream`, or one where max_len <= 2048 (one workgroup per
+ * sequence). SPORK_E_INVAL for bad sizes (1 <= n_min <= n_max <= 32,
+ * 0 <= k <= 4096, 0 <= max_len < 2^31) or a NULL required pointer,
+ * SPORK_E_CAPACITY for a short workspace. */
 int spork_ngram_propose(const int32_t* tokens, const int64_t* seq_off, int32_t n_seqs,
                         int64_t max_len, int32_t n_min, int32_t n_max, int32_t k,
                         int32_t* drafts, int32_t* n_drafts, void* workspace, size_t ws_bytes,
@@ -382,14 +383,14 @@ int spork_ngram_propose(const int32_t* tokens, const int64_t* seq_off, int32_t n
 /* ======================================================================== *
  *  Kernel timing (benchmarks).
  * ======================================================================== */
-#define SPORK_KERNEL_ATTN 0   /* cascade / private-range partial attention */
+#define SPORK_KERNEL_ATTN 0   /* cascade / private-range partial attention (+ the verify step's argmax) */
 #define SPORK_KERNEL_MERGE 1  /* log-sum-exp merge (+ the verify step's accept) */
-#define SPORK_KERNEL_ARGMAX 2 /* greedy argmax over vocabulary chunks */
+#define SPORK_KERNEL_ARGMAX 2 /* greedy argmax of an accept-only call (plan == NULL) */
 #define SPORK_KERNEL_ACCEPT 3 /* accept of an accept-only call (plan == NULL) */
 #define SPORK_KERNEL_CONF_CHUNKS 4 /* confidence: per-chunk argmax and sum of exponentials */
 #define SPORK_KERNEL_CONF_FINAL 5  /* confidence: per-row log-probability and per-probe gate */
 #define SPORK_KERNEL_NGRAM_SCAN 6  /* n-gram drafts: per-chunk longest latest key match */
-#define SPORK_KERNEL_NGRAM_DRAFTS 7 /* n-gram drafts: per-sequence choice and draft copy */
+#define SPORK_KERNEL_NGRAM_DRAFTS 7 /* n-gram drafts: per-sequence choice and draft copy (longer sequences) */
 #define SPORK_KERNEL_READ_CEILING 8 /* streaming-read ceiling (measurement aid) */
 #define SPORK_KERNEL_KINDS 9
 

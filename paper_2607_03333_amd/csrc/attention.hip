@@ -47,23 +47,25 @@ __device__ __forceinline__ float softmax_step(float (&sv)[8], float& m, float& l
 }
 
 // --------------------------------------------------------------------------
-// bf16 partial attention. Persistent workgroups of 4 waves work through lists
-// of units; a unit is a token range of one work item and a slice of its query
+// bf16 partial attention. Persistent workgroups of 4 or 8 waves work through
+// lists of units; a unit is a token range of one work item and a slice of its query
 // rows. The range streams through a ring of LDS slots, one 32-token K/V tile
 // ("stage", 16 KB) each, filled by direct global-to-LDS 16-byte loads
 // (global_load_lds_dwordx4: lane i of an instruction lands at the
 // instruction's LDS base + 16*i), so the stages in flight hold no registers.
-// Each wave issues 4 such loads per stage (waves 0 and 1 the K half, 2 and 3
-// the V half); a barrier publishes the next two stages to all waves and frees
+// Each wave issues 4 such loads per stage, or 2 of 8 waves (the lower half of
+// the waves the K half, the upper one the V half); a barrier publishes the next two stages to all waves and frees
 // the slots read before it. Two kernels share that stream:
 //   narrow (attn_bf16): two workgroups per compute unit, up to 8 16-row tiles
 //     each, 16x16x32 products; decode and short verify rows, bound by HBM.
 //     With 8 waves: one workgroup per compute unit, up to 16 tiles; the
-//     multi-row shapes (long verify, prefill) while their units are short.
+//     multi-row shapes (long verify, prefill) unless all their units suit
+//     the wide kernel.
 //   wide (attn_bf16_wide): one workgroup per compute unit, up to 8 32-row
-//     tiles, 32x32x16 products; the multi-row shapes where the matrix cores
-//     and the instruction issue bound a stage and units are long enough
-//     (kWideStages) to pay for filling and draining its pipeline.
+//     tiles, 32x32x16 products; multi-row shapes whose slices are full, 13 to
+//     16 tiles, and whose units are long enough (kWideStages) to pay for
+//     filling and draining its pipeline. The plan chooses one kernel for all
+//     units.
 //
 // LDS slot layout (1024 chunks of 16 bytes). Bank model (measured on
 // gfx950): 64 banks of 4 bytes, so a 16-byte slot s sits in bank group
@@ -92,8 +94,8 @@ __device__ __forceinline__ float softmax_step(float (&sv)[8], float& m, float& l
 // The wide kernel's layout stands at its head.
 // --------------------------------------------------------------------------
 constexpr int kStageChunks = 1024;  // 32 tokens x (K + V) x 128 channels x 2 bytes / 16
-// LDS stages per workgroup: 4 for two workgroups on a compute unit (narrow),
-// 8 for one (wide). A barrier publishes two stages (narrow: 2 in flight, wide:
+// LDS stages per workgroup: 4 for two workgroups on a compute unit (4 waves),
+// 8 for one (8 waves). A barrier publishes two stages (4 waves: 2 in flight, 8:
 // 6). Against one stage per barrier this halves the barriers, and the waves
 // drift apart inside a pair instead of all reading the same operands right
 // after every barrier: on the narrow loop (with a stage fewer in flight) the
@@ -750,17 +752,18 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) attn_bf16(AttnArgs a
 // Even stages publish the next two, and the loads into the slots this frees
 // are spread over the products up to the next publish.
 //
-// Measured against one or two 16-row tiles per wave of 16x16x32 products whose
-// operands were read in bursts, without the pipeline across stages (same box,
-// in turn): K = 50 verify batch 651 to 623 us (cold inputs 647 to 581),
-// probe prefill 2,780 to 2,676, K = 16 verify batch 273 to 267. Its cycles
-// fell further (1.22 to 0.99 million for K = 50, 5.00 to 4.10 for the prefill,
-// matrix cores busy 35 to 43% and 40 to 50%), but the chip runs these steps at
-// its power limit and lowers the clock as the cycles get denser (2.19 to 1.97
-// and 1.94 to 1.74 GHz).
-// The narrow kernel with 8 waves (scalar block bases, lighter softmax) runs those
-// three batches as fast; this one is ahead where slices are full (see
-// kWideStages in plan.cpp).
+// Measured on batches that the plan sends here (64 query heads on 8 KV heads, us,
+// in turn), against the narrow kernel with 8 waves: 32 sessions of 32,000 tokens,
+// 24 drafts 1,020 against 1,059, a 30-row probe prefill 1,087 against 1,156 (see
+// kWideStages in plan.cpp). Against the loop before both (16-row tiles whose
+// operands were read in bursts, a 64-bit address per lane): 8 sessions of 32,000
+// tokens, 28 drafts 278 against 328, the prefill 287 against 340.
+// The chip runs these steps at its power limit and lowers the clock as the cycles
+// get denser: when the K = 50 verify batch ran here its cycles fell from 1.22 to
+// 0.99 million per launch, but the clock from 2.19 to 1.97 GHz.
+// The stage's variants for the ends of a unit do not fit 256 registers beside the
+// loop's: the compiler spills 45 of them (120 bytes of scratch per lane), outside
+// the loop of FAST pairs.
 // --------------------------------------------------------------------------
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 

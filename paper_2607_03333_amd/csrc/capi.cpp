@@ -457,8 +457,6 @@ int spork_workspace_clear(const spork_plan* plan, void* workspace, size_t ws_byt
   });
 }
 
-// Attention over a plan: the attention launch (with the argmax units of a
-// verify step in its tail), then the merge launch (with the accept).
 // Checks of the attention arguments that come before anything is launched.
 static int check_attention(const spork_plan* plan, const void* dev_image, const void* q, const void* k_cache,
                            const void* v_cache, const void* out) {
@@ -474,6 +472,8 @@ static int check_attention(const spork_plan* plan, const void* dev_image, const 
   return SPORK_OK;
 }
 
+// Attention over a plan: the attention launch (with the argmax units of a
+// verify step in it), then the merge launch (with the accept).
 static int attention(const spork_plan* plan, const void* dev_image, const void* q, const void* k_cache,
                      const void* v_cache, void* out, float* lse, void* workspace, size_t ws_bytes,
                      const spork::AcceptArgs* acc, hipStream_t stream) {

@@ -8,10 +8,11 @@
 
 namespace spork {
 
-// bf16: head_dim 128, 16- or 32-token blocks, workgroups of 4 (narrow) or 8
-// (wide) waves with up to two 16-row tiles per wave; fp32: head_dim 64 or 128, 16- or 32-token
-// blocks, one wave with up to 4 row tiles. The kernel table in
-// attention.hip instantiates exactly these.
+// bf16: head_dim 128, 16- or 32-token blocks, workgroups of 4 or 8 waves with
+// up to two 16-row tiles per wave (8 waves also as the wide kernel, one 32-row
+// tile per wave); fp32: head_dim 64 or 128, 16- or 32-token blocks, one wave
+// with up to 4 row tiles. The kernel table in attention.hip instantiates
+// exactly these.
 bool attention_supported(int32_t dtype, int32_t head_dim, int32_t block_size, int32_t row_tiles, int32_t waves) {
   if (row_tiles < 1 || (block_size != 16 && block_size != 32)) return false;
   if (dtype == 1) {
@@ -24,8 +25,8 @@ bool attention_supported(int32_t dtype, int32_t head_dim, int32_t block_size, in
 }
 
 // Vocabulary chunks per logits row: enough (row, chunk) units for about
-// 2048 workgroups, each chunk at least 8 16-byte loads per thread of a
-// 256-thread workgroup.
+// 2048 workgroups, each chunk at least 8192 logits: 4 (bf16) or 8 (fp32)
+// 16-byte loads per thread of a 256-thread workgroup.
 int32_t accept_chunks(int32_t rows, int32_t vocab) {
   const int32_t max_chunks = vocab / (256 * 8 * 4) > 1 ? vocab / (256 * 8 * 4) : 1;
   int32_t c = rows > 0 ? (2048 + rows - 1) / rows : 1;

@@ -21,7 +21,8 @@ struct Range {
 
 // Relative cost of a 32-token stage of the 8-wave kernel by the row tiles
 // its busiest SIMD holds (tile t is on SIMD t % 4), in 1/1024 of a full one:
-// measured 1,236, 1,560, 1,773 and 2,211 cycles for 1 to 4 tiles.
+// 1,236, 1,560, 1,773 and 2,211 cycles for 1 to 4 tiles, measured on the loop
+// before the present two (not taken again on them).
 constexpr int64_t kStageWeight8[5] = {0, 572, 722, 821, 1024};
 int64_t stage_weight8(int32_t slice_tiles) { return kStageWeight8[std::min(4, (slice_tiles + 3) / 4)]; }
 
