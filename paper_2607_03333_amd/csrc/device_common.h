@@ -89,6 +89,12 @@ __device__ __forceinline__ uint4 load_stream(const uint4* p) {
   return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
 }
 
+// 16 bytes that nothing reads soon: a non-temporal store.
+__device__ __forceinline__ void store_stream(uint4* p, uint4 x) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  __builtin_nontemporal_store(__builtin_bit_cast(u32x4, x), reinterpret_cast<u32x4*>(p));
+}
+
 // Element j of the 16-byte vector u.
 template <typename T>
 __device__ __forceinline__ float vec_f(const uint4& u, int j) {

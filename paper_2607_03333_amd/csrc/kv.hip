@@ -66,10 +66,18 @@ __global__ void __launch_bounds__(256) kv_write_kernel(int hkv, int D, int BS, i
 // different banks (fp32 with 32-token blocks: two lanes per bank).
 // Bound by the stream from and to HBM: 15,001 tokens of 8 heads of 128 bf16
 // channels 149 us by element stores, 38.8 us by blocks, 23.6 us with
-// non-temporal loads, which leave the caches to the stores (calls back to back,
-// whose 123 MB the last-level cache partly holds; cold 25.9 us, 4.7 TB/s).
-// Non-temporal stores too: 21.9 us, but the attention that follows reads the
-// blocks.
+// non-temporal loads (calls over three pools in turn, whose 123 MB each the
+// last-level cache partly holds; cold 25.9 us, 4.7 TB/s).
+// Whole blocks are stored non-temporally too. With ordinary stores the
+// last-level cache is left full of lines still to be written back, and the next
+// step pays for them: the first step over new prompts, ordinary and
+// non-temporal stores, 390 and 318 us (96 unforked sequences of up to 8,191
+// tokens), 278 and 232 (forked decode), 831 and 749 (mixed verify and decode).
+// The write itself, ordinary and non-temporal: bf16, 16-token blocks, 15,001
+// tokens 23.6 and 23.7, 62,500 tokens 103 and 100 (its first call over a new
+// pool 103 and 120); fp32 15,001 48.3 and 46.4; 32-token blocks, bf16
+// 15,001 20.9 and 22.9, fp32 4,000 12.4 and 10.5. A prompt's write and the first
+// decode over it, cold: 8,000 tokens 40.5 and 41.2, 60,000 160 and 147.
 // --------------------------------------------------------------------------
 template <typename T, int D, int BS, int NT>
 __global__ void __launch_bounds__(NT) kv_write_blocks(int hkv, int64_t num_slots, T* kc, T* vc, const int64_t* slots,
@@ -130,12 +138,12 @@ __global__ void __launch_bounds__(NT) kv_write_blocks(int hkv, int64_t num_slots
     uint4* kd = reinterpret_cast<uint4*>(kc + base);
     uint4* vd = reinterpret_cast<uint4*>(vc + base);
 #pragma unroll
-    for (int it = 0; it < KIT; ++it) kd[it * NT + tid] = kr[it];
+    for (int it = 0; it < KIT; ++it) store_stream(kd + it * NT + tid, kr[it]);
 #pragma unroll
     for (int it = 0; it < OIT; ++it) {
       const int d = (it * NT + tid) / QN, q = tid % QN;
       const uint32_t* col = tile + 4 * q * STRIDE + d;
-      vd[it * NT + tid] = make_uint4(col[0], col[STRIDE], col[2 * STRIDE], col[3 * STRIDE]);
+      store_stream(vd + it * NT + tid, make_uint4(col[0], col[STRIDE], col[2 * STRIDE], col[3 * STRIDE]));
     }
     return;
   }

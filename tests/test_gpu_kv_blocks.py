@@ -1,7 +1,8 @@
 """The KV write by whole blocks on both sides of its line between workgroups
 of one wave and of several per block, and what single tokens, each in a block
 of its own, cost on both sides of the line between the scatter by token and
-the write by blocks. Exact against the oracle's scatter."""
+the write by blocks. Exact against the oracle's scatter. And what the write of
+long prompts leaves to the step after it."""
 import numpy as np
 import pytest
 import torch
@@ -70,3 +71,46 @@ def test_single_tokens_at_the_line(bs):
         us[n] = _us(graph.replay) / 20
     say(f"  us {us}")
     assert us[576] <= 1.25 * us[575]
+
+
+def test_a_prompts_write_leaves_no_write_back_to_the_next_step():
+    """The first decode over freshly written prompts against the same decode
+    after a read sweep that evicts whatever the write left in the caches (with
+    ordinary stores: up to 256 MB to be written back, a fifth of this step)."""
+    hkv, d, bs, n, seqs = 8, 128, 16, 8192, 32  # 1.07 GB of K and V
+    nb = seqs * (n // bs + 1)
+    cache = spork.spork_cache_create(nb, bs, np.arange(nb))
+    try:
+        ids = [spork.spork_seq_new(cache) for _ in range(seqs)]
+        slots = [torch.from_numpy(spork.spork_seq_append(cache, s, n)[0]).cuda() for s in ids]
+        shape = spork.make_shape(8 * hkv, hkv, d, bs, spork.SPORK_DTYPE_BF16, d ** -0.5)
+        plan = spork.spork_plan_create(cache, shape, ids, [1] * seqs, list(range(seqs)))
+        image = torch.from_numpy(spork.spork_plan_image(plan)).cuda()
+        work = torch.empty(spork.spork_plan_get_info(plan)["workspace_bytes"], dtype=torch.uint8, device="cuda")
+        spork.spork_workspace_clear(plan, work)
+        kp = torch.zeros((nb, hkv, bs, d), dtype=torch.bfloat16, device="cuda")
+        vp = torch.zeros((nb, hkv, d, bs), dtype=torch.bfloat16, device="cuda")
+        x = torch.randn((n, hkv, d), device="cuda").to(torch.bfloat16)
+        q = torch.randn((seqs, 8 * hkv, d), device="cuda").to(torch.bfloat16)
+        out, lse = torch.empty_like(q), torch.empty((seqs, 8 * hkv), device="cuda")
+        swept = torch.zeros(1 << 28, device="cuda")
+
+        def step(sweep):
+            for s in slots:
+                spork.spork_kv_write(shape, kp, vp, nb, s, x, x)
+            if sweep:
+                swept.amax()
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            spork.spork_attn_decode(plan, image, q, kp, vp, out, lse, work)
+            b.record()
+            torch.cuda.synchronize()
+            return a.elapsed_time(b) * 1e3
+
+        step(False)
+        us = {sweep: float(np.median([step(sweep) for _ in range(9)])) for sweep in (False, True)}
+        say(f"  us right after the write {us[False]:.1f}, on swept caches {us[True]:.1f}")
+        assert us[False] <= 1.1 * us[True]
+    finally:
+        spork.spork_plan_destroy(plan)
+        spork.spork_cache_destroy(cache)
