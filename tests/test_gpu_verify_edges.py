@@ -6,7 +6,8 @@ first mismatches past lane 63 and an all-match), the argmax over the full
 151,936-entry vocabulary on maxima held by +0 and -0, natural (unplanted)
 ties of coarsely rounded, saturating logits, a tie at the last two entries and an all -inf
 row, and the argmax inside the persistent attention launch on a vocabulary
-that is not a multiple of the 16-byte vector (the scalar scan path).
+that is not a multiple of the 16-byte vector (rows that start and end inside
+one).
 """
 import numpy as np
 import pytest
@@ -101,7 +102,7 @@ def test_argmax_signed_zeros_and_natural_ties_full_vocabulary(dtype):
 
 
 def test_argmax_in_the_attention_tail_on_a_ragged_vocabulary():
-    # vocabulary 1001: rows are not 16-byte aligned, the tail units take the
-    # scalar scan path inside the persistent attention launch
+    # vocabulary 1001: rows are not 16-byte aligned, so the tail units of the
+    # persistent attention launch take the ends of rows by element
     wl = synth.make(3, sessions=2, prefix=300, vocab=1001)
     run_workload(wl, "verify V=1001").close()
